@@ -142,6 +142,96 @@ def test_bp_matrix_core_kernel_non_finite(dev, gen):
     assert rel(torch.where(fin, a, 0.0), torch.where(fin, b, 0.0).cpu().numpy()) <= 2 * TOL_OP
 
 
+def positions(g, axis):
+    """t of every pixel at every projection, FP64 [K][n_y][n_x]."""
+    x, y = np.arange(g.n_x) - 0.5 * (g.n_x - 1), np.arange(g.n_y) - 0.5 * (g.n_y - 1)
+    a = np.asarray(g.angles)[:, None, None]
+    return axis + np.cos(a) * x + np.sin(a) * y[:, None]
+
+
+@pytest.mark.parametrize("value", [1e5, 1e6, 1e8, 1e12, 1e30, 3.4028235e38])
+def test_bp_matrix_core_kernel_beside_a_large_bin(dev, gen, value):
+    """One bin far above all others (a dead detector element), in the first, a middle and the last projections: a pixel that
+    it does not touch keeps its own sum.  Bins of 0.2 to 1: every term of the general kernels, and so of the sum, is good
+    to their coordinates (4e-6 bins), and a split term to 2^-21; 1e-5 of the pixel for both."""
+    N, K, S = 125, 61, 1024
+    g, og = pair(nx=N, ny=121, nb=N, K=K, axis=61.7)
+    y = gen.uniform(0.2, 1.0, (S, K, N)).astype(np.float32)
+    hot = [(1, 0, 60), (40, 2, 33), (300, 30, 50), (301, 31, 97), (1022, K - 1, 20), (1023, K - 3, 5)]
+    for s, k, j in hot:
+        y[s, k, j] = value
+    plan = ph.Plan(g, n_slices=S)
+    yt = torch.from_numpy(y).to(dev)
+    a = ph.backproject(plan, yt).double().cpu().numpy()
+    plan.set_bp_slices(1)
+    b = ph.backproject(plan, yt).double().cpu().numpy()
+    assert bool((a != b).any())                         # the matrix-core kernel ran
+    t = positions(g, 61.7)
+    for s, k, j in hot:
+        off = np.abs(t[k] - j) > 1.0 + 1e-4
+        ref = oracle.backproject(y[s], og)
+        for out in (a[s], b[s]):
+            assert np.abs(out - ref)[off].max() <= 1e-5 * ref[off].max(), (s, value)
+            assert (np.abs(out - ref)[off] <= 1e-5 * ref[off]).all(), (s, value)
+            assert np.abs(out - ref)[~off].max() <= 1e-5 * value, (s, value)
+
+
+def test_bp_matrix_core_kernel_wide_range(dev, gen):
+    """Rows that fall by a factor at one bin, pixels on either side of it; slices that begin with zeros or with far smaller
+    values than end them, and the other way round; whole slices near either end of float32; every row or column of another
+    magnitude.  Every pixel is good to 1e-5 of the sum of its own terms' magnitudes, and to what 1e-6 bin (half of it the
+    coordinates' fixed point) changes in them."""
+    N, K, S = 125, 48, 1024
+    g, og = pair(nx=N, ny=121, nb=N, K=K, axis=62.2)
+    y = gen.standard_normal((S, K, N)).astype(np.float32)
+    falls = {3: 1e-4, 4: 1e-7, 5: 1e-9, 6: 1e-12, 7: 1e-20, 8: 1e-30}
+    for s, f in falls.items():
+        y[s, :, 45:] *= np.float32(f)
+    y[20, :10] = 0.0
+    y[21, :10] *= np.float32(1e-25)
+    y[22, 10:] *= np.float32(1e-25)
+    y[23, :5], y[23, 5:] = y[23, :5] * np.float32(1e-33), 0.0
+    y[23, 40, 50] = 3e38
+    y[24] *= np.float32(1e-33)
+    y[25] *= np.float32(1e35)
+    y[26] *= (10.0 ** gen.uniform(-30, 0, (K, 1))).astype(np.float32)
+    y[27] *= (10.0 ** gen.uniform(-30, 0, (1, N))).astype(np.float32)
+    plan = ph.Plan(g, n_slices=S)
+    out = ph.backproject(plan, torch.from_numpy(y).to(dev)).double().cpu().numpy()
+    t = positions(g, 62.2)
+
+    def difference(rows, t):    # of the two bins of every pixel, summed
+        q = np.pad(rows.astype(np.float64), ((0, 0), (1, 2)))
+        j = np.clip(np.floor(t).astype(int) + 1, 0, N + 1).reshape(K, -1)
+        d = np.abs(np.take_along_axis(q, j + 1, 1) - np.take_along_axis(q, j, 1)).reshape(t.shape)
+        return np.where((t >= -1.0) & (t < N), d, 0.0)
+
+    for s in [0, *falls, *range(20, 28)]:
+        change = np.maximum(difference(y[s], t - 1e-6), difference(y[s], t + 1e-6)).sum(0)
+        bound = 1e-5 * oracle.backproject(np.abs(y[s]), og) + 1e-6 * change
+        assert (np.abs(out[s] - oracle.backproject(y[s], og)) <= bound).all(), s
+
+
+def test_bp_matrix_core_kernel_all_large_and_nan_columns(dev, gen):
+    """A column of the detector that is dead in every projection and slice, and one that is NaN in some: most pixels are
+    summed apart from the matrix product, with an accumulating beta."""
+    N, K, S = 125, 24, 1024
+    g, og = pair(nx=N, ny=121, nb=N, K=K, axis=62.3)   # (no pixel lies on a bin at any angle)
+    y = gen.uniform(0.2, 1.0, (S, K, N)).astype(np.float32)
+    y[:, :, 30] = 1e15
+    y[100:200, :, 80] = float("nan")
+    yt = torch.from_numpy(y).to(dev)
+    base = torch.from_numpy(gen.uniform(0.0, 1.0, (S, 121, N)).astype(np.float32)).to(dev)
+    plan = ph.Plan(g, n_slices=S)
+    a = ph.backproject(plan, yt, out=base.clone(), alpha=0.75, beta=0.5)
+    plan.set_bp_slices(1)
+    b = ph.backproject(plan, yt, out=base.clone(), alpha=0.75, beta=0.5)
+    assert bool((torch.isnan(a) == torch.isnan(b)).all())
+    clear = torch.from_numpy((np.abs(positions(g, 62.3) - 30) > 1.0001).all(0)).to(dev) & torch.isfinite(b)
+    assert int(clear.sum()) > 1000 * S
+    assert bool(((a - b).abs()[clear] <= 2e-5 * b.abs()[clear]).all())
+
+
 def test_cp_primal_step_on_matrix_cores(dev, gen):
     """The fused Chambolle-Pock primal step of a plan of many slices (32 of 500 x 509) against the one-slice kernel."""
     g, og = pair(nx=500, ny=509, nb=510, K=7, axis=254.0, shifts=0.3)
