@@ -158,7 +158,8 @@ int pyhst_plan_get_fp_kernel(const pyhst_plan *plan, int32_t *kind);
  * else two from two slices on), 1 = one, 2 = two where the plan allows it.  Two
  * slices share each staged window entry (one 16-byte LDS read per pixel update
  * of both) and the coordinate arithmetic; the images equal one slice per
- * workgroup bit for bit.  The matrix-core kernel sums the same hat weights and
+ * workgroup with the same tile bit for bit (1 and 2 may choose different
+ * automatic tiles on large plans, and 0 tile 5 on small ones).  The matrix-core kernel sums the same hat weights and
  * rows as pairs of f16 halves in FP32 (error against exact sums below the
  * others').  EARG for another value. */
 int pyhst_plan_set_bp_slices(pyhst_plan *plan, int32_t per_workgroup);

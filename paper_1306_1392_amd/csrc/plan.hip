@@ -51,10 +51,11 @@ int choose_tile(const pyhst_plan &p, bool primal)
     // too few 32x32 tiles for 2 workgroups per CU (a single 256^2 slice has 64): split the projections
     // of each tile over 4 angle groups instead; two slices per workgroup (not in the primal step) halve the
     // tiles' number, so there up to 3 of one slice's (8 x 256^2 x 360, 2 per CU, 108 -> 53 us; 3 x 512^2 x 90, 3
-    // per CU, 30 -> 27; 6 x 362^2 x 90, 3.4 per CU, would go from 30 to 34), up to 2 where the projections are few
-    // (4 x 392^2 x 55, 2.6 per CU, would go from 20 to 23)
+    // per CU, 28 -> 25; 6 x 362^2 x 90, 3.4 per CU, would go from 30 to 34), up to 2 where the projections are few
+    // (2.3 to 3 per CU break even at 70 projections: 4 x 392^2 x 55 would go from 20 to 23, x 80 from 26 to 25).  Angle
+    // groups hold one slice and add in another order: not where two per workgroup are asked for
     const int64_t few = p.max_K >= 90 ? 3LL * p.cu_count : 2LL * p.cu_count;
-    if (p.n_items[3] < 2LL * p.cu_count || (!primal && two_slice_bp(p) && p.n_items[3] <= few)) return 5;
+    if (p.n_items[3] < 2LL * p.cu_count || (!primal && p.bp_slices == 0 && two_slice_bp(p) && p.n_items[3] <= few)) return 5;
     return 3;
 }
 

@@ -535,6 +535,21 @@ def test_bp_tile_rule_for_few_pairs(dev, gen, n, S, K, tile):
     assert rel(out[at], oracle.backproject(y[at], og)) <= TOL_OP
 
 
+@pytest.mark.parametrize("n,S,K", [(256, 8, 90), (256, 9, 30), (256, 12, 90), (500, 3, 120)])
+def test_bp_two_slices_asked_for_with_few_pairs(dev, gen, n, S, K):
+    """Where the automatic choice may take angle groups, two slices per workgroup are still what is run when they are asked
+    for: the tile of one slice per workgroup, and its image bit for bit."""
+    g, og = pair(nx=n, ny=n, nb=n, K=K, axis=0.49 * n)
+    plan = ph.Plan(g, n_slices=S)
+    y = torch.from_numpy(gen.standard_normal((S, K, n)).astype(np.float32)).to(dev)
+    outs = []
+    for per in (1, 2):
+        plan.set_bp_slices(per)
+        outs.append((plan.get_tiles()[0], ph.backproject(plan, y)))
+    assert outs[0][0] == outs[1][0]
+    assert bool((outs[0][1] == outs[1][1]).all())
+
+
 def test_fbp_batch_equals_single(dev, gen):
     g, _ = pair(**CASES["odd_shift"])
     plan4 = ph.Plan(g, n_slices=4)
