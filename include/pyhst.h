@@ -126,7 +126,12 @@ int pyhst_plan_sizes(const pyhst_plan *plan, int64_t *sino_elems, int64_t *filt_
  * the projections split over 4 angle groups (1024-thread workgroups, partial sums added in a fixed
  * order; for slices too small to fill the chip with tiles); -1 = automatic.
  * persistent != 0 runs the backprojector as one persistent launch over a
- * cost-sorted (slice, tile) work list. */
+ * cost-sorted (slice, tile) work list.  get_tiles returns the tile that plain
+ * backprojections run with, also where it was chosen automatically, or -1
+ * where they run on the matrix cores (see pyhst_plan_set_bp_slices), which only
+ * the automatic tile does: set_tiles with what get_tiles returned leaves them
+ * as they were.  (The Chambolle-Pock step's automatic choice may be another;
+ * a tile that is set holds for both.) */
 int pyhst_plan_set_tiles(pyhst_plan *plan, int32_t bp_tile, int32_t persistent);
 int pyhst_plan_get_tiles(const pyhst_plan *plan, int32_t *bp_tile, int32_t *persistent);
 /* Forward-projector kernel for every projection this plan makes (forward_project,
@@ -165,7 +170,9 @@ int pyhst_plan_get_fp_kernel(const pyhst_plan *plan, int32_t *kind);
 int pyhst_plan_set_bp_slices(pyhst_plan *plan, int32_t per_workgroup);
 /* Autotuner: times the backprojector of this plan for every tile shape, with
  * and without the persistent work queue (reps launches each, HIP events on
- * `stream`), on filt (filtered layout) -> img, and keeps the fastest.  Writes
+ * `stream`), and for the automatic tile where that runs on the matrix cores, on
+ * filt (filtered layout) -> img, and keeps the fastest (get_tiles tells which,
+ * -1 being the last).  Writes
  * img; synchronises the stream; *best_ms (may be NULL) receives the time of one
  * launch with the chosen setting. */
 int pyhst_plan_autotune(pyhst_plan *plan, const float *filt, float *img, int32_t reps, float *best_ms,

@@ -744,7 +744,7 @@ int pyhst_plan_get_fp_kernel(const pyhst_plan *p, int32_t *kind)
 int pyhst_plan_get_tiles(const pyhst_plan *p, int32_t *bp_tile, int32_t *persistent)
 {
     if (!p) return fail(PYHST_EARG, "get_tiles: plan is NULL");
-    if (bp_tile) *bp_tile = choose_tile(*p);
+    if (bp_tile) *bp_tile = bpm_applies(*p) ? -1 : choose_tile(*p);   // (the matrix-core kernel has no tile shape to choose)
     if (persistent) *persistent = p->persistent;
     return PYHST_OK;
 }

@@ -232,6 +232,34 @@ def test_bp_matrix_core_kernel_all_large_and_nan_columns(dev, gen):
     assert bool(((a - b).abs()[clear] <= 2e-5 * b.abs()[clear]).all())
 
 
+def test_bp_tiles_read_and_set_keep_the_kernel(dev, gen):
+    """set_tiles(*get_tiles()) changes nothing: a plan on the matrix cores reports -1, as created and after an autotune; one
+    with a set tile, one that is too small and one of other slices per workgroup report a tile."""
+    g, og = pair(nx=125, ny=121, nb=125, K=90, axis=62.3)
+    S = 1024
+    y = torch.from_numpy(gen.standard_normal((S, 90, 125)).astype(np.float32)).to(dev)
+    plan = ph.Plan(g, n_slices=S)
+    first = ph.backproject(plan, y)
+    assert plan.get_tiles() == (-1, 0)
+    for tune in (False, True):
+        if tune:
+            plan.autotune(y, torch.empty_like(first), reps=3)
+            first = ph.backproject(plan, y)
+        plan.set_tiles(*plan.get_tiles())
+        assert bool((ph.backproject(plan, y) == first).all()), tune
+    plan.set_tiles(-1, False)
+    plan.set_bp_slices(2)
+    assert plan.get_tiles()[0] >= 0
+    plan.set_bp_slices(0)
+    plan.set_tiles(3, False)
+    assert plan.get_tiles() == (3, 0)
+    assert ph.Plan(g, n_slices=4).get_tiles()[0] >= 0
+    small = ph.Plan(g, n_slices=40)
+    out = ph.backproject(small, y[:40])
+    small.set_tiles(*small.get_tiles())
+    assert bool((ph.backproject(small, y[:40]) == out).all())
+
+
 def test_cp_primal_step_on_matrix_cores(dev, gen):
     """The fused Chambolle-Pock primal step of a plan of many slices (32 of 500 x 509) against the one-slice kernel."""
     g, og = pair(nx=500, ny=509, nb=510, K=7, axis=254.0, shifts=0.3)
