@@ -1067,11 +1067,11 @@ def main():
     stream.synchronize()
     filt_ms = ev2[0].elapsed_time(ev2[1]) / nbp
     del sino_f
-    # roofline: many slices with the automatic tile run on the matrix cores, bound by their LDS reads; else the two-slice
+    # roofline: where the plan runs on the matrix cores (it then reports no tile), their LDS reads; else the two-slice
     # backprojector reads 8 LDS bytes per update (one 16-byte read per pixel, projection and slice pair) against the
     # 16-byte read port (256 B/clk/CU), with the VALU mix (4 lane-ops/update) beside it
     csrc = os.path.join(ROOT, "paper_1306_1392_amd", "csrc")
-    matrix = R >= 32 and args.tile < 0
+    matrix = tile < 0
     lds_bytes = BPM_LDS_BYTES_PER_UPDATE if matrix else BP_LDS_BYTES_PER_UPDATE
     lds_peak = LDS4_PEAK_GBS if matrix else LDS_PEAK_GBS
     lds_achieved = lds_bytes * U / (bp_ms * 1e-3) / 1e9
@@ -1087,6 +1087,7 @@ def main():
     if matrix:
         tflops = BPM_FLOPS_PER_UPDATE * U / (bp_ms * 1e-3) / 1e12
         res["roofline"]["matrix"] = {"achieved_tflops": round(tflops, 1), "flops_per_update": BPM_FLOPS_PER_UPDATE,
+                                     "operands": "f32 values as two f16 halves, summed in f32",
                                      "peak_tflops": MFMA_F16_PEAK_TFLOPS,
                                      "frac": round(tflops / MFMA_F16_PEAK_TFLOPS, 4)}
     else:
