@@ -232,6 +232,24 @@ def test_bp_matrix_core_kernel_all_large_and_nan_columns(dev, gen):
     assert bool(((a - b).abs()[clear] <= 2e-5 * b.abs()[clear]).all())
 
 
+@pytest.mark.parametrize("ny,nx,S", [(121, 125, 1024), (128, 97, 1024), (65, 1001, 256), (1001, 65, 256), (500, 511, 48)])
+def test_cp_primal_step_on_matrix_cores_sizes(dev, gen, ny, nx, S):
+    """The primal step's quads of pixels at the image's edges, last columns that are not a whole quad, more slices than a
+    multiple of 32: against the one-slice kernel and the oracle."""
+    g, og = pair(nx=nx, ny=ny, nb=90, K=5, axis=44.3, s=0.9)
+    y = gen.standard_normal((S, 5, 90)).astype(np.float32)
+    yt, res = torch.from_numpy(y).to(dev), []
+    for per in (0, 1):
+        plan = ph.Plan(g, n_slices=S)
+        plan.set_bp_slices(per)
+        res.append(ph.reconstruct_slices(plan, sino=yt, method=ph.TV_CP, lam=0.05, n_iter=3, op_norm=60.0))
+    assert bool((res[0] != res[1]).any())               # the matrix-core kernel ran
+    for s in (0, S // 2, S - 1):
+        ref = oracle.cp_tv(y[s].astype(np.float64), og, 0.05, 3, 60.0)
+        assert rel(res[0][s], ref) <= TOL_PIPE and rel(res[1][s], ref) <= TOL_PIPE, s
+    assert rel(res[0], res[1].cpu().numpy()) <= TOL_PIPE
+
+
 def test_bp_tiles_read_and_set_keep_the_kernel(dev, gen):
     """set_tiles(*get_tiles()) changes nothing: a plan on the matrix cores reports -1, as created and after an autotune; one
     with a set tile, one that is too small and one of other slices per workgroup report a tile."""
