@@ -250,6 +250,28 @@ def test_cp_primal_step_on_matrix_cores_sizes(dev, gen, ny, nx, S):
     assert rel(res[0], res[1].cpu().numpy()) <= TOL_PIPE
 
 
+@pytest.mark.parametrize("S,K", [(1024, 5), (1003, 33), (1007, 70)])
+def test_bp_matrix_core_kernel_sums_apart(dev, gen, S, K):
+    """Pixels summed apart from the matrix product: more and fewer slices than go side by side, marked ones among others,
+    sums over less than, just more than and some chunks of projections; and in the primal step (one Chambolle-Pock
+    iteration from zero is a multiple of the backprojection)."""
+    g, og = pair(nx=125, ny=121, nb=100, K=K, axis=49.3)
+    y = gen.uniform(0.2, 1.0, (S, K, 100)).astype(np.float32)
+    hot = sorted(set(gen.integers(0, S, 60)) | {0, 1, 2, S - 1})
+    y[hot, :, 40] = 1e13
+    yt = torch.from_numpy(y).to(dev)
+    far = (np.abs(positions(g, 49.3) - 40) > 1.0001).all(0)
+    assert far.sum() > 200
+    out = ph.backproject(ph.Plan(g, n_slices=S), yt).cpu().numpy()
+    step = ph.reconstruct_slices(ph.Plan(g, n_slices=S), sino=yt, method=ph.TV_CP, lam=0.05, n_iter=1, op_norm=60.0)
+    step = step.cpu().numpy()
+    for s in hot + [3, S // 2]:
+        ref = oracle.backproject(y[s], og)[far]
+        assert np.abs(out[s][far] / ref - 1.0).max() <= 1e-5, s
+        r = step[s][far] / ref
+        assert np.abs(r / np.median(step[3][far] / oracle.backproject(y[3], og)[far]) - 1.0).max() <= 2e-5, s
+
+
 def test_bp_tiles_read_and_set_keep_the_kernel(dev, gen):
     """set_tiles(*get_tiles()) changes nothing: a plan on the matrix cores reports -1, as created and after an autotune; one
     with a set tile, one that is too small and one of other slices per workgroup report a tile."""
