@@ -157,16 +157,17 @@ int pyhst_plan_get_fp_kernel(const pyhst_plan *plan, int32_t *kind);
  * (backproject, the FBP, the ISTA / FISTA and patch-prior steps; the
  * Chambolle-Pock step with its fused primal update keeps one): 0 = automatic
  * (on a uniform plan without the persistent work queue: with the automatic tile,
- * pixels of at most one bin, and enough slices and tiles to fill it (16, 24 to
- * 32, 48 and more slices), the matrix-core kernel, 16 or 32 slices per
- * workgroup, for every backprojection,
- * else two from two slices on), 1 = one, 2 = two where the plan allows it.  Two
- * slices share each staged window entry (one 16-byte LDS read per pixel update
- * of both) and the coordinate arithmetic; the images equal one slice per
- * workgroup with the same tile bit for bit (1 and 2 may choose different
- * automatic tiles on large plans, and 0 tile 5 on small ones).  The matrix-core kernel sums the same hat weights and
- * rows as pairs of f16 halves in FP32 (error against exact sums below the
- * others').  EARG for another value. */
+ * pixels of at most one bin, and enough slices, tiles and projections that its
+ * workgroups of 16 or 32 slices are the faster ones, the matrix-core kernel, also
+ * for the Chambolle-Pock step, else two from two slices on), 1 = one, 2 = two
+ * where the plan allows it.  Two slices share each staged window entry (one
+ * 16-byte LDS read per pixel update of both) and the coordinate arithmetic; the
+ * images equal one slice per workgroup with the same tile bit for bit (1 and 2
+ * may choose different automatic tiles on large plans, and 0 tile 5 on small
+ * ones).  The matrix-core kernel sums the same hat weights and rows as pairs of
+ * f16 halves in FP32, with coordinates in fixed point; pixels that infinite, NaN
+ * or far larger bins beside their own would spoil are summed in FP32 apart (error
+ * against exact sums below the others').  EARG for another value. */
 int pyhst_plan_set_bp_slices(pyhst_plan *plan, int32_t per_workgroup);
 /* Autotuner: times the backprojector of this plan for every tile shape, with
  * and without the persistent work queue (reps launches each, HIP events on

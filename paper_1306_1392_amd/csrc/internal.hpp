@@ -137,8 +137,8 @@ int choose_tile(const pyhst_plan &p, bool primal = false);   // primal: for the 
 constexpr bool reg_filter_length(int P) { return P >= 256 && P <= 4096; }
 // whether plain backprojections (no fused primal step) of this plan run two slices per workgroup
 bool two_slice_bp(const pyhst_plan &p);
-// whether backprojections of this plan run on the matrix cores (k_bpm.hip)
-bool bpm_applies(const pyhst_plan &p);
+// whether plain backprojections (primal: the Chambolle-Pock primal step) of this plan run on the matrix cores (k_bpm.hip)
+bool bpm_applies(const pyhst_plan &p, bool primal = false);
 // persistent-work counter of `st` on this plan (nullptr once every slot is taken)
 int *stream_counter(const pyhst_plan &p, hipStream_t st);
 

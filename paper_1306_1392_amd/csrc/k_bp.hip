@@ -533,7 +533,7 @@ hipError_t launch_mode(const pyhst_plan &p, int cfg, const float *sino, int filt
 hipError_t launch_backproject(const pyhst_plan &p, const float *sino, int filtered, float *img, float alpha,
                               float beta, const CpPrimal *cp, hipStream_t st)
 {
-    if (bpm_applies(p)) return launch_bpm(p, sino, filtered, img, alpha, beta, cp, st);
+    if (bpm_applies(p, cp != nullptr)) return launch_bpm(p, sino, filtered, img, alpha, beta, cp, st);
     const int cfg = choose_tile(p, cp != nullptr);
     if (cp) return launch_mode<1>(p, cfg, sino, filtered, img, alpha, 0.0f, *cp, st);
     CpPrimal none{};

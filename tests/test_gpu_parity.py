@@ -250,6 +250,40 @@ def test_cp_primal_step_on_matrix_cores_sizes(dev, gen, ny, nx, S):
     assert rel(res[0], res[1].cpu().numpy()) <= TOL_PIPE
 
 
+@pytest.mark.parametrize("S,case", [(1000, dict(nx=101, ny=97, nb=104, K=41, axis=51.3, shifts=0.4)),
+                                    (60, dict(nx=430, ny=417, nb=431, K=62, axis=214.0)),
+                                    (62, dict(nx=540, ny=556, nb=310, K=110, axis=280.0, scan=2)),
+                                    (16, dict(nx=800, ny=800, nb=577, K=90, axis=287.2, s=0.7)),
+                                    (48, dict(nx=1024, ny=1017, nb=800, K=49, axis=399.5))])
+def test_bp_matrix_core_kernel_where_it_is_chosen(dev, gen, S, case):
+    """Plans that run on the matrix cores (get_tiles says so): every slice against the one-slice kernel, and sampled ones
+    against the oracle, both to the operator tolerances; half acquisition, small pixels, odd sizes, a rest of 16 slices."""
+    g, og = pair(**case)
+    plan = ph.Plan(g, n_slices=S)
+    assert plan.get_tiles()[0] == -1
+    y = gen.standard_normal((S, g.n_angles, g.n_det)).astype(np.float32)
+    y *= (10.0 ** gen.uniform(-6, 6, S)).astype(np.float32)[:, None, None]
+    yt = torch.from_numpy(y).to(dev)
+    a = ph.backproject(plan, yt)
+    plan.set_bp_slices(1)
+    b = ph.backproject(plan, yt)
+    d = ((a - b).double().flatten(1).norm(dim=1) / b.double().flatten(1).norm(dim=1)).max()
+    assert 0.0 < float(d) <= 2 * TOL_OP
+    for s in (0, S // 2, S - 1):
+        assert rel(a[s], oracle.backproject(y[s], og)) <= TOL_OP, s
+
+
+@pytest.mark.parametrize("S,n,K,matrix", [
+    (60, 512, 120, True), (28, 600, 200, True), (32, 512, 90, True), (64, 2048, 1800, True), (1024, 256, 180, True),
+    (24, 640, 300, False), (48, 430, 300, False), (64, 1100, 14, False), (520, 101, 61, False), (33, 2048, 100, False)])
+def test_bp_matrix_core_rule(dev, S, n, K, matrix):
+    """Which of the two kernels a plan's backprojections run on, well on either side of where they take the same time."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rule counts compute units")
+    g, _ = pair(nx=n, ny=n, nb=n, K=K, axis=0.5 * (n - 1))
+    assert (ph.Plan(g, n_slices=S).get_tiles()[0] == -1) == matrix
+
+
 @pytest.mark.parametrize("S,K", [(1024, 5), (1003, 33), (1007, 70)])
 def test_bp_matrix_core_kernel_sums_apart(dev, gen, S, K):
     """Pixels summed apart from the matrix product: more and fewer slices than go side by side, marked ones among others,
