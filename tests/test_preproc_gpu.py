@@ -90,6 +90,22 @@ def test_ring_filter_parity(dev):
     assert rel(got, oracle.ring_filter(sino, 12, obj=obj)) <= TOL_OP
 
 
+@pytest.mark.parametrize("K", [2, 16, 17, 50])
+@pytest.mark.parametrize("width", [0, 1, 150, 700])
+def test_ring_filter_rows_and_widths(dev, K, width):
+    """One workgroup for all rows of 256 bins, and several, narrow windows and ones wider than the detector; an infinite bin
+    reaches the bins whose window holds it."""
+    rng = np.random.default_rng(K + width)
+    sino = rng.standard_normal((2, K, 520)).astype(np.float32)
+    plan = ph.Plan(ph.Geometry(8, 8, 520, np.arange(K) * np.pi / K, 259.5), n_slices=2)
+    got = ph.ring_filter(plan, torch.from_numpy(sino).to(dev), width)
+    assert np.abs(got.cpu().numpy() - oracle.ring_filter(sino, width)).max() <= 1e-6   # a float32 difference of values under 5
+    sino[1, 0, 300] = np.inf
+    got = ph.ring_filter(plan, torch.from_numpy(sino).to(dev), width).cpu().numpy()
+    near = np.abs(np.arange(520) - 300) <= width
+    assert not np.isfinite(got[1][:, near]).any() and np.isfinite(got[1][:, ~near]).all() and np.isfinite(got[0]).all()
+
+
 @pytest.fixture(scope="module")
 def ringed_raw():
     R, N, K = 3, 64, 90
