@@ -998,26 +998,35 @@ bool fp_unit(const pyhst_plan &p)
 constexpr double FP_COS45 = 0.7071067;   // (rounded down) the least |a| / s
 
 // Frames of 64 positions (fp_frame_kernel): pixels of a quarter of a bin to one bin, 32-bit byte offsets within a slice.
-// They are the faster choice (staged or, below half a bin, line kernel against frames: 2 x 512^2 x 90 pixels of one bin
-// 41 and 26 us, 12 x 256^2 x 90 45 and 37; half a bin 55 and 26, 57 and 38; 0.3 bins 207 and 29, 439 and 44) except
-//   with pixels of 0.943 to one bin, where several slices share the staged kernel's weights: from 16 slices on
-//   (32 x 512^2 x 90: 273 and 285 us), or where the projections are dense enough for full groups, a third of
-//   the image's width or more (8 x 1024^2 x 720: 1440 and 1970; 6 x 600^2 x 250 208 and 217; below, 5 x 1024^2 x 90 300
-//   and 187, 12 x 800^2 x 180 466 and 465);
-//   for many small slices with pixels of half a bin or more (32 x 128^2 x 60, half a bin: 24 and 30).
+// Against the staged (below half a bin the line or block) kernel, 3000 plans of 1 to 200 slices, 16 to 1600 pixels and 8 to
+// 1000 projections were timed with either; of those that the lines below let in 1 in 170 is slower by more than 3 %,
+// the worst by 11 %.  One slice: always.  Else
+//   pixels of 0.943 to one bin, where several slices share the staged kernel's weights: from 64 pixels on (15 x 49^2 x 853
+//   25 us staged, 49 here), while one slice and projection per workgroup would fill the chip 24 times (a small image: 4
+//   times), or with projections that are few for the width (2 x 1270^2 x 395 443 and 560; 5 x 1024^2 x 90 300 and 187);
+//   16 slices and more are the staged kernel's (32 x 512^2 x 90 273 and 285);
+//   from half a bin: up to 15 slices, unless the image is small and the projections many (4 x 93^2 x 410 18 and 21); more
+//   slices of large images, unless their projections are few (71 x 1196^2 x 11 955 and 1730) or, near half a bin, many;
+//   below: unless there are many small slices of pixels near half a bin (67 x 117^2 x 760 448 and 503).
 bool fp_frames(const pyhst_plan &p)
 {
     double s_min = 1e300, s_max = 0.0;
-    int n = 0;
+    int n = 0, nb = 0;
     for (const auto &g : p.gd) {
         s_min = std::min(s_min, g.s);
         s_max = std::max(s_max, g.s);
         n = std::max({n, g.nx, g.ny});
+        nb = std::max(nb, (int)g.nb);
         if ((int64_t)(g.ny + 32 * FR_L) * g.nx > (1 << 29) - 2 * FR_FAR) return false;
     }
     if (s_max > 1.0 || s_min < 0.25 || n > FR_FAR / 4) return false;
-    if (fp_unit(p)) return p.n_slices == 1 || (p.n_slices < 16 && (p.fp_max_grp <= 2 || 3 * p.max_K < n));
-    return fp_nc(p) == 0 || p.n_slices < 16 || n >= 256;
+    const int S = p.n_slices;
+    const double K = (double)p.max_K, fill = S * K * ((nb + 63) / 64) / p.cu_count;
+    if (S == 1) return true;
+    if (fp_unit(p)) return S < 16 && n >= 64 && (fill <= (n >= 128 ? 24.0 : 4.0) || 3.0 * K * std::sqrt((double)S) < n);
+    if (fp_nc(p) == 0) return S < 64 || n >= 128 || s_min < 0.4;
+    if (S < 16) return n >= 100 || fill <= 6.0;
+    return n >= 256 && K >= 32 && (s_min >= 0.55 || K < 200);
 }
 
 template <int MODE>

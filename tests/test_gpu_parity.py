@@ -452,6 +452,24 @@ def test_fp_frames(dev, gen, ny, nx, nb, K, s, S):
     assert rel(out, ph.forward_project(plan, t).cpu().numpy()) <= 2e-6
 
 
+@pytest.mark.parametrize("ny,nx,nb,K,s,S", [
+    (64, 63, 70, 20, 1.0, 5), (63, 63, 70, 20, 1.0, 5), (128, 100, 140, 300, 1.0, 5), (128, 100, 140, 800, 1.0, 5),
+    (300, 301, 310, 70, 1.0, 15), (300, 301, 310, 70, 1.0, 16), (99, 90, 70, 300, 0.6, 4), (100, 90, 70, 300, 0.6, 4),
+    (260, 256, 150, 40, 0.56, 17), (260, 256, 150, 31, 0.56, 17), (60, 50, 20, 30, 0.41, 70), (60, 50, 20, 30, 0.3, 70)])
+def test_fp_either_side_of_the_frames_rule(dev, gen, ny, nx, nb, K, s, S):
+    """Plans of several slices that the frames take and their neighbours that they do not: the oracle's projections, and
+    the line kernel's in every slice."""
+    g, og = pair(nx=nx, ny=ny, nb=nb, K=K, axis=0.48 * (nb - 1), s=s)
+    x = gen.standard_normal((S, ny, nx)).astype(np.float32)
+    xt = torch.from_numpy(x).to(dev)
+    plan = ph.Plan(g, n_slices=S)
+    out = ph.forward_project(plan, xt)
+    plan.set_fp_kernel(ph.FP_LINES)
+    assert rel(out, ph.forward_project(plan, xt).cpu().numpy()) <= 2 * TOL_OP
+    for i in (0, S - 1):
+        assert rel(out[i], oracle.forward_project(x[i:i + 1], og)[0]) <= TOL_OP, i
+
+
 def test_fp_frames_uneven_and_non_finite(dev, gen):
     """Slices of their own sizes in one launch; an infinite or NaN pixel reaches the bins that it adds to, and none
     further than two bins from it (a lane's three sums hold |t - bin| <= 2; so do the staged kernel's candidates)."""
