@@ -592,7 +592,10 @@ struct PatchCall {
     hipError_t step(float *W, float invL, float thr, float mom, hipStream_t st)
     {
         const int64_t M = (int64_t)S * np;
-        if (!mfma_fits(G, DT, M, na, mm)) {
+        // the product's wavefronts each take 32 patches with all atoms: few patches leave most of the chip out of the shrink
+        // step, whose own launch spreads it (50 patches x 128 atoms 39 us a step apart, 47 as one; 128 and 96 atoms break
+        // even near 3000 patches, 64 near 500, 32 are ahead with any)
+        if (!mfma_fits(G, DT, M, na, mm) || (na > 32 && M < 64 * na)) {
             hipError_t er = gradient(Z, true, st);
             if (er != hipSuccess) return er;
             shrink_kernel<<<grid_n(nw), 256, 0, st>>>(grad, Z, W, nw, invL, thr, mom, a.fast);

@@ -148,3 +148,23 @@ def test_patch_step_atom_counts(dev, na, fast):
     assert not W1[..., na].any() and W0.any()
     assert float((W0 - W1[..., :na]).norm() / W0.norm()) <= 1e-5
     assert float((x0 - x1).norm() / x0.norm()) <= 1e-5
+
+
+@pytest.mark.parametrize("na", [32, 64, 96, 128])
+@pytest.mark.parametrize("n", [113, 147])
+def test_patch_step_patch_counts(dev, na, n):
+    """Fewer and more patches than the fused product and shrink step asks for (64 an atom, from 64 atoms on): equal to the
+    general kernels (one zero atom more) within the rounding of four steps."""
+    rng = np.random.default_rng(na + n)
+    g = ph.Geometry(n, n, n, np.arange(5) * np.pi / 5, 0.49 * n)
+    plan = ph.Plan(g, n_slices=2)
+    y = torch.from_numpy(rng.standard_normal((2, 5, n)).astype(np.float32)).to(dev)
+    D = torch.from_numpy((rng.standard_normal((na + 1, 64)) / 8.0).astype(np.float32)).to(dev)
+    D[na] = 0.0
+    kw = dict(fast=True, lipschitz=400.0)
+    stride = 3 if na == 64 else 2
+    x1, W1 = ph.patch_fista(plan, y, D, 8, stride, 0.3, 0.05, 4, **kw)
+    x0, W0 = ph.patch_fista(plan, y, D[:na].contiguous(), 8, stride, 0.3, 0.05, 4, **kw)
+    assert bool(W0.any()) and not bool(W1[..., na].any())
+    assert float((W0 - W1[..., :na]).norm() / W0.norm()) <= 1e-5
+    assert float((x0 - x1).norm() / x0.norm()) <= 1e-5
