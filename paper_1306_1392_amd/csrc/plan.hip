@@ -39,11 +39,19 @@ int choose_tile(const pyhst_plan &p, bool primal)
     const int64_t want = 4LL * p.cu_count;
     if (two_slice_bp(p)) {
         // two slices per workgroup: 64 x 64 tiles (64 x 2048^2 x 1800: 41.0 ms, against 41.5 with 64 x 128
-        // and 44.2 with 64 x 32), while their pairs still give 4 workgroups per CU (an odd last slice is a pair:
-        // 7 x 1000^2 x 721 0.65 ms with 64 x 64 tiles, 0.71 with 64 x 32)
-        const int64_t pairs = (p.n_slices + 1) / 2;
-        for (const int c : {0, 1, 3})
-            if (p.n_items[c] / p.n_slices * pairs >= want) return c;
+        // and 44.2 with 64 x 32), while their pairs still give 4 workgroups per CU.  An odd last slice is a pair that costs
+        // as much as the others; where only it makes up the number, 64 x 64 tiles take part if no CU holds a workgroup
+        // more than most (7 x 1000^2 x 721, 1024: 0.65 ms, with 64 x 32 0.71; but 9 x 1023 x 798 x 210, 1040: 204 and 189 us;
+        // 3 x 1650^2 x 490, 1352: 690 and 550), 64 x 32 tiles up to 7 slices if few do (1.0 to 1.4 times the 32 x 32
+        // tiles' speed; but 5 x 852 x 792 x 339, 1050: 198 and 169 us, 13 x 530^2 x 489 281 and 236)
+        const int64_t pairs = (p.n_slices + 1) / 2, cu = p.cu_count;
+        for (const int c : {0, 1, 3}) {
+            const int64_t n = p.n_items[c] / p.n_slices * pairs;
+            if (n < want) continue;
+            const int64_t full = 100 * n / ((n + cu - 1) / cu * cu);   // percent of the last workgroups' round
+            if (p.n_items[c] >= 2 * want || c == 3) return c;
+            if (c == 0 ? n <= 5 * cu && full >= 98 : p.n_slices <= 7 && full >= 85) return c;
+        }
     }
     if (p.n_items[4] >= want) return 4;
     if (p.n_items[0] >= want) return 0;
@@ -52,9 +60,10 @@ int choose_tile(const pyhst_plan &p, bool primal)
     // of each tile over 4 angle groups instead; two slices per workgroup (not in the primal step) halve the
     // tiles' number, so there up to 3 of one slice's (8 x 256^2 x 360, 2 per CU, 108 -> 53 us; 3 x 512^2 x 90, 3
     // per CU, 28 -> 25; 6 x 362^2 x 90, 3.4 per CU, would go from 30 to 34), up to 2 where the projections are few
-    // (2.3 to 3 per CU break even at 70 projections: 4 x 392^2 x 55 would go from 20 to 23, x 80 from 26 to 25).  Angle
-    // groups hold one slice and add in another order: not where two per workgroup are asked for
-    const int64_t few = p.max_K >= 90 ? 3LL * p.cu_count : 2LL * p.cu_count;
+    // (2.3 to 3 per CU break even at 70 projections: 4 x 392^2 x 55 would go from 20 to 23, x 80 from 26 to 25; 2 per CU at
+    // 45, up to 3 us apart below it: 8 x 256^2 x 20 12 and 9), less than 2 for next to none.  Angle groups hold one slice and
+    // add in another order: not where two per workgroup are asked for
+    const int64_t few = p.max_K >= 90 ? 3LL * p.cu_count : p.max_K >= 9 ? 2LL * p.cu_count : 0;
     if (p.n_items[3] < 2LL * p.cu_count || (!primal && p.bp_slices == 0 && two_slice_bp(p) && p.n_items[3] <= few)) return 5;
     return 3;
 }

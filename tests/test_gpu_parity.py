@@ -232,7 +232,7 @@ def test_bp_matrix_core_kernel_all_large_and_nan_columns(dev, gen):
     assert bool(((a - b).abs()[clear] <= 2e-5 * b.abs()[clear]).all())
 
 
-@pytest.mark.parametrize("ny,nx,S", [(121, 125, 1024), (128, 97, 1024), (65, 1001, 256), (1001, 65, 256), (500, 511, 48)])
+@pytest.mark.parametrize("ny,nx,S", [(121, 125, 1024), (128, 97, 1024), (65, 1001, 256), (1001, 65, 256), (500, 511, 62)])
 def test_cp_primal_step_on_matrix_cores_sizes(dev, gen, ny, nx, S):
     """The primal step's quads of pixels at the image's edges, last columns that are not a whole quad, more slices than a
     multiple of 32: against the one-slice kernel and the oracle."""
@@ -653,6 +653,21 @@ def test_bp_tile_rule_for_few_pairs(dev, gen, n, S, K, tile):
     out = ph.backproject(plan, torch.from_numpy(y).to(dev))
     at = [0, S // 2, S - 1]
     assert rel(out[at], oracle.backproject(y[at], og)) <= TOL_OP
+
+
+@pytest.mark.parametrize("n,w,S,K,tile", [(1000, 1000, 7, 6, 0), (1023, 798, 9, 6, 1), (1650, 1650, 3, 6, 1), (530, 530, 13, 12, 3),
+                                          (735, 735, 7, 12, 1), (852, 792, 5, 12, 3), (256, 256, 8, 8, 3)])
+def test_bp_tile_rule_for_odd_slices(dev, gen, n, w, S, K, tile):
+    """Tiles of plans where the odd last slice makes up the number of workgroups, or with next to no projections; a sampled
+    slice, the last among them, holds the projector's transpose."""
+    g, og = pair(nx=n, ny=w, nb=n, K=K, axis=0.49 * n)
+    plan = ph.Plan(g, n_slices=S)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert plan.get_tiles()[0] == tile
+    y = gen.standard_normal((S, K, n)).astype(np.float32)
+    out = ph.backproject(plan, torch.from_numpy(y).to(dev))
+    for s in (0, S - 1):
+        assert rel(out[s], oracle.backproject(y[s], og)) <= TOL_OP, s
 
 
 @pytest.mark.parametrize("n,S,K", [(256, 8, 90), (256, 9, 30), (256, 12, 90), (500, 3, 120)])
