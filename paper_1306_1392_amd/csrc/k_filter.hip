@@ -85,6 +85,8 @@ __global__ __launch_bounds__(256) void normalize_kernel(const uint16_t *__restri
 // in one piece.  A workgroup takes 256 bins of HS_ROWS rows of a radiograph and computes each transmission once, into
 // LDS (with a border of one; absent pixels are +inf): a thread that made its nine itself spent its time on their
 // divisions and loads (7 rows x 721 x 1003: 67 us, now 35, most of it the sorting network and the logarithm).
+// Of radiographs with one or two rows a workgroup takes these, four or two times as many bins (1 row x 1973 x 1295:
+// 20.6 us, with four rows and 256 bins 27, without LDS 20).
 constexpr int HS_ROWS = 4;
 
 __device__ inline float transmission(const uint16_t *raw, const float *f0, const float *f1, const float *dk, float a,
@@ -103,66 +105,70 @@ __device__ inline void cswap(float &a, float &b)
     b = hi;
 }
 
+template <int HS>
 __global__ __launch_bounds__(256) void normalize_hotspot_kernel(const uint16_t *__restrict__ raw,
                                                                 const float *__restrict__ flats, FlatInfo fi,
                                                                 const float *__restrict__ dark, float eps, float thr,
                                                                 int K, int R, int R_in, int h0, int nb, int n_rb,
                                                                 float *__restrict__ out)
 {
-    __shared__ float t_[HS_ROWS + 2][258];
-    __shared__ bool dead_[HS_ROWS + 2][258];
-    const int k = blockIdx.x / n_rb, r0 = (blockIdx.x - k * n_rb) * HS_ROWS;   // projection, first output row
-    const int j0 = blockIdx.y * 256;
+    __shared__ float t_[HS + 2][258];
+    __shared__ bool dead_[HS + 2][258];
+    const int k = blockIdx.x / n_rb, r0 = (blockIdx.x - k * n_rb) * HS;   // projection, first output row
     int i0, i1;
     float a;
     flat_interp(fi, k, i0, i1, a);
     const uint16_t *img = raw + (int64_t)k * R_in * nb;      // radiograph k, [R_in][nb]
     const float *f0 = flats + (int64_t)i0 * R_in * nb, *f1 = flats + (int64_t)i1 * R_in * nb;
-    for (int i = threadIdx.x; i < (HS_ROWS + 2) * 258; i += 256) {
-        const int q = i / 258, c = i - q * 258;
-        const int rr = r0 + h0 + q - 1, jj = j0 + c - 1;
-        bool dead = false;
-        const bool in = rr >= 0 && rr < R_in && jj >= 0 && jj < nb;
-        t_[q][c] = in ? transmission(img, f0, f1, dark, a, (int64_t)rr * nb + jj, dead) : INFINITY;
-        dead_[q][c] = dead;
-    }
-    __syncthreads();
-    const int j = j0 + threadIdx.x, c = threadIdx.x + 1;
-    if (j >= nb) return;
+    for (int b = 0; b < HS_ROWS / HS; ++b) {
+        const int j0 = (blockIdx.y * (HS_ROWS / HS) + b) * 256;
+        if (j0 >= nb) return;                            // uniform over the workgroup
+        if (b > 0) __syncthreads();
+        for (int i = threadIdx.x; i < (HS + 2) * 258; i += 256) {
+            const int q = i / 258, c = i - q * 258;
+            const int rr = r0 + h0 + q - 1, jj = j0 + c - 1;
+            bool dead = false;
+            const bool in = rr >= 0 && rr < R_in && jj >= 0 && jj < nb;
+            t_[q][c] = in ? transmission(img, f0, f1, dark, a, (int64_t)rr * nb + jj, dead) : INFINITY;
+            dead_[q][c] = dead;
+        }
+        __syncthreads();
+        const int j = j0 + threadIdx.x, c = threadIdx.x + 1;
 #pragma unroll
-    for (int q = 1; q <= HS_ROWS; ++q) {
-        const int r = r0 + q - 1, ri = r + h0;
-        if (r >= R) break;
-        float *dst = out + ((int64_t)r * K + k) * nb;
-        float t = t_[q][c];
-        if (dead_[q][c]) {
-            dst[j] = 0.0f;
-            continue;
-        }
-        float v[8] = {t_[q - 1][c - 1], t_[q - 1][c], t_[q - 1][c + 1], t_[q][c - 1],
-                      t_[q][c + 1], t_[q + 1][c - 1], t_[q + 1][c], t_[q + 1][c + 1]};
-        const int nr = (ri > 0) + 1 + (ri + 1 < R_in), nc = (j > 0) + 1 + (j + 1 < nb);
-        const int n = nr * nc - 1;   // neighbours that exist
-        // sorting network for 8 values (absent neighbours are +inf and sort last)
-        cswap(v[0], v[1]); cswap(v[2], v[3]); cswap(v[4], v[5]); cswap(v[6], v[7]);
-        cswap(v[0], v[2]); cswap(v[1], v[3]); cswap(v[4], v[6]); cswap(v[5], v[7]);
-        cswap(v[1], v[2]); cswap(v[5], v[6]); cswap(v[0], v[4]); cswap(v[3], v[7]);
-        cswap(v[1], v[5]); cswap(v[2], v[6]);
-        cswap(v[1], v[4]); cswap(v[3], v[6]);
-        cswap(v[2], v[4]); cswap(v[3], v[5]);
-        cswap(v[3], v[4]);
-        float lo = v[0], hi = v[0];
+        for (int q = 1; q <= HS; ++q) {
+            const int r = r0 + q - 1, ri = r + h0;
+            if (r >= R || j >= nb) break;
+            float *dst = out + ((int64_t)r * K + k) * nb;
+            float t = t_[q][c];
+            if (dead_[q][c]) {
+                dst[j] = 0.0f;
+                continue;
+            }
+            float v[8] = {t_[q - 1][c - 1], t_[q - 1][c], t_[q - 1][c + 1], t_[q][c - 1],
+                          t_[q][c + 1], t_[q + 1][c - 1], t_[q + 1][c], t_[q + 1][c + 1]};
+            const int nr = (ri > 0) + 1 + (ri + 1 < R_in), nc = (j > 0) + 1 + (j + 1 < nb);
+            const int n = nr * nc - 1;   // neighbours that exist
+            // sorting network for 8 values (absent neighbours are +inf and sort last)
+            cswap(v[0], v[1]); cswap(v[2], v[3]); cswap(v[4], v[5]); cswap(v[6], v[7]);
+            cswap(v[0], v[2]); cswap(v[1], v[3]); cswap(v[4], v[6]); cswap(v[5], v[7]);
+            cswap(v[1], v[2]); cswap(v[5], v[6]); cswap(v[0], v[4]); cswap(v[3], v[7]);
+            cswap(v[1], v[5]); cswap(v[2], v[6]);
+            cswap(v[1], v[4]); cswap(v[3], v[6]);
+            cswap(v[2], v[4]); cswap(v[3], v[5]);
+            cswap(v[3], v[4]);
+            float lo = v[0], hi = v[0];
 #pragma unroll
-        for (int i = 1; i < 8; ++i) {
-            if (i == (n - 1) / 2) lo = v[i];
-            if (i == n / 2) hi = v[i];
+            for (int i = 1; i < 8; ++i) {
+                if (i == (n - 1) / 2) lo = v[i];
+                if (i == n / 2) hi = v[i];
+            }
+            if (n > 0) {
+                const float med = (n & 1) ? hi : 0.5f * (lo + hi);
+                if (t - med > thr) t = med;
+            }
+            if (!(t >= eps)) t = eps;
+            dst[j] = -logf(t);
         }
-        if (n > 0) {
-            const float med = (n & 1) ? hi : 0.5f * (lo + hi);
-            if (t - med > thr) t = med;
-        }
-        if (!(t >= eps)) t = eps;
-        dst[j] = -logf(t);
     }
 }
 
@@ -739,10 +745,15 @@ hipError_t launch_normalize_hotspot(const pyhst_plan &p, const uint16_t *raw, co
 {
     const GeoDev &g = p.gd[0];
     const int R = p.n_slices;
-    const int n_rb = (R + HS_ROWS - 1) / HS_ROWS;
-    normalize_hotspot_kernel<<<dim3((unsigned)((int64_t)g.K * n_rb), (g.nb + 255) / 256), 256, 0, st>>>(
-        raw, flats, make_flats(flat_pos, n_flats), dark, eps, thr, g.K, R, halo_lo + R + halo_hi, halo_lo, g.nb, n_rb, sino);
-    return hipGetLastError();
+    auto run = [&](auto kernel, int rows) {
+        const int n_rb = (R + rows - 1) / rows;
+        const int bins = 256 * (HS_ROWS / rows);
+        kernel<<<dim3((unsigned)((int64_t)g.K * n_rb), (g.nb + bins - 1) / bins), 256, 0, st>>>(
+            raw, flats, make_flats(flat_pos, n_flats), dark, eps, thr, g.K, R, halo_lo + R + halo_hi, halo_lo, g.nb, n_rb, sino);
+        return hipGetLastError();
+    };
+    return R == 1 ? run(normalize_hotspot_kernel<1>, 1) : R == 2 ? run(normalize_hotspot_kernel<2>, 2)
+                                                                 : run(normalize_hotspot_kernel<HS_ROWS>, HS_ROWS);
 }
 
 hipError_t launch_ring_filter(const pyhst_plan &p, float *sino, const float *obj, int width, double *work,

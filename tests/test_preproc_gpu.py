@@ -90,6 +90,31 @@ def test_ring_filter_parity(dev):
     assert rel(got, oracle.ring_filter(sino, 12, obj=obj)) <= TOL_OP
 
 
+@pytest.mark.parametrize("N", [5, 256, 257, 1300])
+def test_hotspot_chunks_of_one_and_two_rows(dev, N):
+    """Chunks of one, two and three rows with their halo rows equal the whole radiographs, bit for bit, at bins on either side
+    of a workgroup's; the whole equals the oracle wherever the decision is not within rounding."""
+    R, K = 6, 7
+    rng = np.random.default_rng(N)
+    raw = rng.integers(3000, 30000, (K, R, N)).astype(np.uint16)
+    flats = rng.uniform(38000, 42000, (2, R, N)).astype(np.float32)
+    dark = rng.uniform(90, 110, (R, N)).astype(np.float32)
+    dark[2, N // 2] = 50000.0                      # a bin without light
+    pos, ang = np.array([0.0, 6.0]), np.arange(K) * np.pi / K
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    plan = lambda S: ph.Plan(ph.Geometry(8, 8, N, ang, (N - 1) / 2), n_slices=S)
+    whole = ph.normalize_hotspot(plan(R), put(raw), put(flats), pos, put(dark), 0.1)
+    ref = oracle.normalize_hotspot(raw, flats, pos, dark, 0.1)
+    assert (np.abs(whole.cpu().numpy() - ref) > 1e-5).mean() <= 1e-3
+    for rows in (1, 2, 3):
+        for r in range(0, R, rows):
+            lo, hi = min(r, 1), min(R - r - rows, 1)
+            part = slice(r - lo, r + rows + hi)
+            got = ph.normalize_hotspot(plan(rows), put(raw[:, part]), put(flats[:, part]), pos, put(dark[part]), 0.1,
+                                       halo=(lo, hi))
+            assert bool((got == whole[r:r + rows]).all()), (rows, r)
+
+
 @pytest.mark.parametrize("K", [2, 16, 17, 50])
 @pytest.mark.parametrize("width", [0, 1, 150, 700])
 def test_ring_filter_rows_and_widths(dev, K, width):
