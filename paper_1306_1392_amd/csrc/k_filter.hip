@@ -763,10 +763,10 @@ hipError_t launch_ring_filter(const pyhst_plan &p, float *sino, const float *obj
     const int S = p.n_slices, K = g.K, L = g.nb;
     ring_mean_kernel<<<dim3((L + 63) / 64, S), 1024, 0, st>>>(sino, obj, K, L, work);
     const dim3 grid((L + 255) / 256, (K + RING_ROWS - 1) / RING_ROWS, S);
-    // The window is summed once for all rows, in a launch of its own, unless one workgroup holds them all: summed by each
-    // workgroup again, 64 slices x 1800 x 2048 take 0.76 ms with half-width 8, 1.6 with 64 and 8.4 with 600, here 0.58,
+    // The window is summed once for all rows, in a launch of its own, unless every workgroup has a compute unit of its own
+    // (3 x 24 x 54 9.5 us, apart 13): summed by each workgroup again, 64 slices x 1800 x 2048 take 0.76 ms with half-width 8, 1.6 with 64 and 8.4 with 600, here 0.58,
     // 0.59 and 0.63 (a row per workgroup: 1.31, 1.32 and 1.40); 7 x 721 x 1003 with 8 22 us and 22 (204).
-    if (K > RING_ROWS) {
+    if ((int64_t)grid.x * grid.y * grid.z > p.cu_count) {
         double *hp = work + (int64_t)S * L;
         ring_highpass_kernel<<<dim3((L + 255) / 256, S), 256, 0, st>>>(work, L, width, hp);
         ring_subtract_kernel<true><<<grid, 256, 0, st>>>(sino, hp, K, L, 0);
