@@ -829,7 +829,7 @@ typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // Grid: (projections rounded up to whole rounds of the 8 XCDs, chunks, slices).
 template <int MODE, int FR_W>
-__global__ __launch_bounds__(64 * FR_W) void fp_frame_kernel(Tables T, const float *__restrict__ img,
+__global__ __launch_bounds__(64 * FR_W, 6) void fp_frame_kernel(Tables T, const float *__restrict__ img,
                                                              float *__restrict__ out, float alpha, CpDual cp)
 {
     __shared__ __attribute__((aligned(16))) float tile[FR_W][FR_L * FR_LD];
@@ -969,15 +969,45 @@ __global__ __launch_bounds__(64 * FR_W) void fp_frame_kernel(Tables T, const flo
         part[i] = v;
     }
     __syncthreads();
-    const int b = threadIdx.x, j = j0 + b;
-    if (b >= B || j >= nb) return;
+    if (wv > 0) return;                              // (a chunk has fewer than 64 bins)
+    const int b = lane, j = j0 + b;
+    const bool mine = b < B && j < nb;
     float tot = 0.0f;
-    for (int l = max(0, (int)((float)(b - 1) * (float)inv) - 1); l < 64; ++l) {
-        const int n = b + 1 - tab_o[0][l];
-        if (n < 0) break;
-        if (n <= 2) tot += part[n * 64 + l];
+    if (mine)
+        for (int l = max(0, (int)((float)(b - 1) * (float)inv) - 1); l < 64; ++l) {
+            const int n = b + 1 - tab_o[0][l];
+            if (n < 0) break;
+            if (n <= 2) tot += part[n * 64 + l];
+        }
+    // A sum that is not finite is taken over the pixels that touch the bin alone: a lane of the frames holds three bins for
+    // each of its pixels, and an infinite or NaN pixel times the weight 0 reaches one bin too many.
+    auto touching = [&](int bin, int l) {            // line l's share
+        const double u = ((double)(j0 + bin) - (g.axis + T.shiftd[g.ang_off + k]) + a * ci + bb * (cl - l)) / a;
+        const double lo = fmax(ceil(u - inv), 0.0), hi = fmin(u + inv, n_pos - 1.0);
+        double v = 0.0;
+        for (double q = lo; q <= hi; q += 1.0) {
+            const double w = 1.0 - fabs(a * (q - u));
+            if (w > 0.0) v += w * im[(int64_t)l * (rows ? nx : 1) + (int64_t)q * (rows ? 1 : nx)];
+        }
+        return v;
+    };
+    bool bad = mine && !(fabsf(tot) < INFINITY);
+    if (__ballot(bad)) {
+        // (images of NaN only: found on one of these lines by most bins at once; a NaN stays one)
+        if (bad)
+            for (int i = 1; i < 8 && bad; i += 3) bad = !isnan(touching(b, n_lines * i / 8));
+        if (mine && !bad && !(fabsf(tot) < INFINITY)) tot = NAN;
+        for (unsigned long long again = __ballot(bad); again; again &= again - 1) {
+            const int bin = __ffsll(again) - 1;
+            double sum = 0.0;
+            for (int l = lane; l - lane < n_lines && __ballot(sum != sum) == 0; l += 64)
+                if (l < n_lines) sum += touching(bin, l);
+            for (int d = 32; d; d >>= 1) sum += __shfl_xor(sum, d);
+            if (lane == bin) tot = (float)sum;
+        }
     }
-    fp_store<MODE>(cp, out, sd.sino_off + (int64_t)k * nb + j, alpha * (float)(g.s * g.s) * tot, (int64_t)slice * nb + j);
+    if (mine)
+        fp_store<MODE>(cp, out, sd.sino_off + (int64_t)k * nb + j, alpha * (float)(g.s * g.s) * tot, (int64_t)slice * nb + j);
 }
 
 int fp_nc(const pyhst_plan &p)

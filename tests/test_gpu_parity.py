@@ -470,6 +470,29 @@ def test_fp_either_side_of_the_frames_rule(dev, gen, ny, nx, nb, K, s, S):
         assert rel(out[i], oracle.forward_project(x[i:i + 1], og)[0]) <= TOL_OP, i
 
 
+@pytest.mark.parametrize("s", [1.0, 0.95, 0.7, 0.5, 0.45, 0.3])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_fp_frames_non_finite_reach(dev, gen, s, value):
+    """In the frames an infinite or NaN pixel reaches the bins that it touches, as itself, and no others; these hold the
+    projection of the rest."""
+    n, nb, K = 180, int(200 * s), 37
+    g, og = pair(nx=n, ny=n - 7, nb=nb, K=K, axis=0.49 * nb, s=s, jitter=0.3, shifts=0.3)
+    x = gen.uniform(0.1, 1.0, (1, n - 7, n)).astype(np.float32)
+    rest = x.copy()
+    hit = np.zeros((K, nb), bool)
+    for iy, ix in [(5, 9), (90, 100), (172, 30), (60, 179)]:
+        x[0, iy, ix], rest[0, iy, ix] = value, 0.0
+        t = 0.49 * nb + g.axis_shift + s * (np.cos(g.angles) * (ix - (n - 1) / 2) + np.sin(g.angles) * (iy - (n - 8) / 2))
+        d = np.abs(t[:, None] - np.arange(nb))
+        assert np.abs(d - 1.0).min() > 1e-5 and np.abs(d).min() > 1e-5
+        hit |= d < 1.0
+    out = ph.forward_project(ph.Plan(g), torch.from_numpy(x).to(dev))[0].cpu().numpy()
+    assert bool((np.isfinite(out) == ~hit).all())
+    assert np.isnan(out[hit]).all() if np.isnan(value) else (out[hit] == value).all()
+    clean = oracle.forward_project(rest, og)[0]
+    assert np.abs(out - clean)[~hit].max() <= 1e-5 * np.abs(clean).max()
+
+
 def test_fp_frames_uneven_and_non_finite(dev, gen):
     """Slices of their own sizes in one launch; an infinite or NaN pixel reaches the bins that it adds to, and none
     further than two bins from it (a lane's three sums hold |t - bin| <= 2; so do the staged kernel's candidates)."""
