@@ -12,10 +12,12 @@
   the persistent and general forms, the fused first two convolutions, the fused level-0 up-sampling,
   the weight-gradient kernel (staging, 8 x 8 transposes, operands, bias sums), the up-sampling kernels
   (operands and output coverage) and the half-wave exchange of the epilogues.
-* prox_step2_kernel (two fused ROF dual steps on a 64 x 16 tile with a two-pixel halo): its loops,
-  replayed with NaN-initialised LDS so that a read of an unset entry fails, equal two plain single steps
-  exactly, on ragged and degenerate image shapes.
-* filter4096_kernel: its index arithmetic, LDS layout and table lookups against numpy's FFT.
+* prox_march_kernel (up to five ROF dual steps in flight down a strip of 64 columns): its recurrence, lane shifts, strips
+  and segments equal as many plain steps on ragged and degenerate image shapes, every result written once.
+* filter_rows (the ramp filter's register FFT, 256 to 4096 points): index arithmetic, LDS layout with NaN-initialised
+  entries, twiddle and spectrum lookups against numpy's FFT.
+* The matrix-core backprojector's operands: what is left of a bin and of a term by the f16 halves.
+test_prox2_emulation and test_fft4096_register_emulation replay forms of the first two of these that the kernels had before.
 """
 import math
 
@@ -959,3 +961,189 @@ def test_fft4096_register_emulation():
     ref = np.fft.ifft(np.fft.fft(x) * Hnat)
     assert not np.isnan(y).any()
     np.testing.assert_allclose(y, ref, rtol=0, atol=1e-10 * np.abs(ref).max())
+
+
+# ------------------------------------------------------------------ register FFT of the ramp filter, P = 256 R
+def _bits(x, n):
+    return int(f"{x:0{n}b}"[::-1], 2) if n else 0
+
+
+def _dft_small(v, inv):
+    """R-point DFT over axis 1, natural order (the kernel's dft<R> for R < 16)."""
+    R = v.shape[1]
+    w = np.exp((2j if inv else -2j) * np.pi * np.outer(np.arange(R), np.arange(R)) / R)
+    return v @ w
+
+
+@pytest.mark.parametrize("R", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("lg_over", [0, 1, 3])
+def test_register_filter_replay(R, lg_over):
+    """filter_rows: 16 / R row pairs of a workgroup with their parts of LDS (NaN-initialised: a read of an unset entry
+    shows), its strides, the twiddles as products of table values of a table 2^lg_over times as long as the transform's, and
+    the thread's 16 neighbouring values of the bit-reversed spectrum: equals ifft(fft(x) H) for rows of up to P / 2 points."""
+    M, LG = 16 * R, {1: 0, 2: 1, 4: 2, 8: 3, 16: 4}[R]
+    P = 256 * R
+    S1 = 256 if R == 16 else 17 * R
+    T2 = R if R <= 2 else R + 1
+    S2 = {1: 0, 2: 34, 4: 84, 8: 152, 16: 272}[R]
+    pair = 16 * max(S1, S2)
+    lds = {r: 16 // r * 16 * max(256 if r == 16 else 17 * r, {1: 0, 2: 34, 4: 84, 8: 152, 16: 272}[r]) for r in (1, 2, 4, 8, 16)}
+    assert lds[4] == max(lds.values()) and lds[4] * 8 <= 65536     # what a workgroup of an uneven plan has
+    rng = np.random.default_rng(R + lg_over)
+    tab = P << lg_over
+    tw = np.exp(-2j * np.pi * np.arange(tab // 2) / tab)
+    Hnat = rng.standard_normal(P)
+    Hnat[1:] = (Hnat[1:] + Hnat[:0:-1]) / 2                        # real and even
+    H = np.array([Hnat[_bits(n, 8 + LG)] for n in range(P)]) / P   # the plan's table: bit-reversed, 1/P folded
+    z = np.full(16 // R * pair, np.nan + 0j)
+    tid = np.arange(256)
+    f, u = tid // M, tid % M
+    zb = f * pair
+    x = np.zeros((16 // R, P), complex)
+    x[:, :P // 2] = rng.standard_normal((16 // R, P // 2)) + 1j * rng.standard_normal((16 // R, P // 2))
+    v = x[f[:, None], u[:, None] + M * np.arange(16)]
+    assert not v[:, 8:].any()
+    k1, c0 = u // R, u % R
+    sh = lg_over
+    for i in range(4):
+        assert ((u << i) << sh).max() < tab // 2 and (((16 * c0) << i) << sh).max() < tab // 2
+    b1w = [tw[(u << i) << sh] for i in range(4)]
+    b2w = [tw[((16 * c0) << i) << sh] for i in range(4)]
+    at = np.array([_bits(k, 4) for k in k1]) * 16 * R + 16 * c0
+    assert (at % 4 == 0).all() and at.max() + 16 <= P
+    h = H[at[:, None] + np.arange(16)]
+    v = _dft16(v, False)
+    for k in range(16):
+        z[zb + k * S1 + u] = v[:, _rev4(k)] * _wpow(b1w, k)
+    v = _dft16(np.stack([z[zb + k1 * S1 + c0 + R * d] for d in range(16)], 1), False)
+    if R == 1:
+        w = np.stack([v[:, _rev4(b)] * h[:, _bits(b, 4)] for b in range(16)], 1)
+        w = _dft16(w, True)
+        z[:] = np.nan
+        for d in range(16):
+            z[zb + k1 * S1 + d] = w[:, _rev4(d)]
+    else:
+        z[:] = np.nan
+        for b in range(16):
+            z[zb + k1 * S2 + b * T2 + c0] = v[:, _rev4(b)] * _wpow(b2w, b)
+        bs = np.array([[_bits(int(16 // R * c + i), 4) for i in range(16 // R)] for c in c0])
+        rows = [np.stack([z[zb + k1 * S2 + bs[:, i] * T2 + c] for c in range(R)], 1) for i in range(16 // R)]
+        z[:] = np.nan
+        for i in range(16 // R):
+            X = _dft_small(rows[i], False)
+            w = np.stack([X[:, b2] * h[:, i * R + _bits(b2, LG)] for b2 in range(R)], 1)
+            w = _dft_small(w, True)
+            for c in range(R):
+                z[zb + k1 * S2 + bs[:, i] * T2 + c] = w[:, c]
+        v = np.stack([z[zb + k1 * S2 + b * T2 + c0] * np.conj(_wpow(b2w, b)) for b in range(16)], 1)
+        v = _dft16(v, True)
+        z[:] = np.nan
+        for d in range(16):
+            z[zb + k1 * S1 + c0 + R * d] = v[:, _rev4(d)]
+    v = _dft16(np.stack([z[zb + k * S1 + u] * np.conj(_wpow(b1w, k)) for k in range(16)], 1), True)
+    y = np.full((16 // R, P), np.nan + 0j)
+    for m in range(8):
+        y[f, u + M * m] = v[:, _rev4(m)]
+    ref = np.fft.ifft(np.fft.fft(x, axis=1) * Hnat, axis=1)[:, :P // 2]
+    np.testing.assert_allclose(y[:, :P // 2], ref, rtol=0, atol=1e-10 * np.abs(ref).max())
+
+
+# ------------------------------------------------------------------ marching ROF dual steps
+def _march(T, first, last, H, p1, p2, g, il, tau, lam):
+    """prox_march_kernel over one image: every strip and segment, its 64 lanes as an array.  Outputs start as NaN and are
+    written once each (asserted)."""
+    ny, nx = g.shape
+    W = 64 - 2 * T - 1
+    out = np.full((1 if last else 2, ny, nx), np.nan)
+    lane = np.arange(64)
+    shr = lambda a: np.concatenate([[0.0], a[:-1]])     # the column to the left, zero into the first lane
+    shl = lambda a: np.concatenate([a[1:], [0.0]])
+    for bx in range(-(-nx // W)):
+        for seg in range(-(-ny // H)):
+            ya, yb = seg * H, min(seg * H + H, ny)
+            x = bx * W - (T + 1) + lane
+            inside, right = (x >= 0) & (x < nx), x + 1 < nx
+            mine = inside & (lane > T) & (lane < 64 - T)
+            xc = np.where(inside, x, 0)
+            P1, P2, V = (np.zeros((T, 64)) for _ in range(3))
+            C1, C2, G0, G1 = (np.zeros((T + 1, 64)) for _ in range(4))
+            L2 = np.zeros(64)
+            r0, r1 = max(ya - T - 1, 0), yb + 2 * T - 1
+            for r in range(r0, r0 + -(-(r1 - r0) // 4) * 4):
+                ok, row = inside & (r < ny), min(r, ny - 1)
+                C1[0] = np.where(ok, 0.0 if first else p1[row, xc], 0.0)
+                C2[0] = np.where(ok, 0.0 if first else p2[row, xc], 0.0)
+                G0[0] = np.where(ok, g[row, xc], 0.0)
+                for s in range(T - 1, -1, -1):
+                    y = r - 2 * s - 1
+                    c1, c2 = C1[s].copy(), C2[s].copy()
+                    nv = -G0[s] * il + (c1 - shr(c1)) + (c2 - P2[s])
+                    ov = V[s].copy()
+                    a = np.where(right, shl(ov) - ov, 0.0)
+                    b = nv - ov if y + 1 < ny else np.zeros(64)
+                    m = 1.0 + tau * np.sqrt(a * a + b * b)
+                    C1[s + 1] = np.where(inside, (P1[s] + tau * a) / m, 0.0)
+                    C2[s + 1] = (P2[s] + tau * b) / m if y >= 0 else 0.0
+                    P1[s], P2[s], V[s] = c1, c2, nv
+                    G0[s + 1] = G1[s]
+                    G1[s] = G0[s]
+                y = r - 2 * T + 1
+                if last:
+                    u = G0[T] - lam * ((C1[T] - shr(C1[T])) + (C2[T] - L2))
+                    L2 = C2[T].copy()
+                if ya <= y < yb:
+                    for q, val in enumerate([u] if last else [C1[T], C2[T]]):
+                        assert np.isnan(out[q, y, x[mine]]).all()
+                        out[q, y, x[mine]] = val[mine]
+    return out
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("ny,nx,H", [(1, 1, 16), (1, 130, 16), (70, 1, 16), (17, 53, 16), (33, 54, 16), (64, 61, 32), (50, 107, 16)])
+def test_prox_march_replay(T, ny, nx, H):
+    """The steps in flight of a strip (rows behind one another, lane shifts, margins of a segment) equal T plain steps on the
+    whole image: from zero, from a dual field whose last column and row are zero, and with the result as the last step."""
+    rng = np.random.default_rng(T * 1000 + ny + nx)
+    g = rng.standard_normal((ny, nx))
+    lam, tau = 0.3, 0.125
+    p1, p2 = 0.3 * rng.standard_normal((ny, nx)), 0.3 * rng.standard_normal((ny, nx))
+    p1[:, -1], p2[-1] = 0.0, 0.0
+    for first in (True, False):
+        q1, q2 = (np.zeros_like(g), np.zeros_like(g)) if first else (p1, p2)
+        for _ in range(T):
+            q1, q2 = _step(q1, q2, g, 1 / lam, tau)
+        k = _march(T, first, False, H, p1, p2, g, 1 / lam, tau, lam)
+        np.testing.assert_allclose(k[0], q1, rtol=0, atol=1e-13)
+        np.testing.assert_allclose(k[1], q2, rtol=0, atol=1e-13)
+        u = _march(T, first, True, H, p1, p2, g, 1 / lam, tau, lam)[0]
+        np.testing.assert_allclose(u, g - lam * _div(q1, q2), rtol=0, atol=1e-13)
+
+
+# ------------------------------------------------------------------ operands of the matrix-core backprojector
+def _f16(x):
+    with np.errstate(over="ignore"):
+        return np.asarray(x, np.float16).astype(np.float64)
+
+
+def test_matrix_core_operand_split():
+    """Rows as f16 halves h and 2^11 (v - h), weights as halves of 2^11 w, the products of the three: a bin of 2^-15 in the
+    scale or more keeps 2^-21 of itself, a smaller one 2^-36 of the scale, and the term 2^-20 of itself."""
+    rng = np.random.default_rng(0)
+    v = np.ldexp(rng.uniform(0.5, 1.0, 200000), rng.integers(-45, 16, 200000)).astype(np.float32).astype(np.float64)
+    v *= rng.choice([-1.0, 1.0], v.size)
+    h = _f16(v)
+    l = _f16(2048.0 * v - 2048.0 * h)
+    assert np.isfinite(h).all() and np.isfinite(l).all()
+    err = np.abs(h + l / 2048.0 - v)
+    big = np.abs(v) >= 2.0 ** -15
+    assert (err[big] <= 2.0 ** -21 * np.abs(v[big])).all() and (err <= np.maximum(2.0 ** -36, 2.0 ** -21 * np.abs(v))).all()
+    assert (err[np.abs(v) >= 1.0] <= 2.0 ** -24 * 2 * np.abs(v[np.abs(v) >= 1.0])).all()
+    w = 2048.0 * rng.integers(0, 1 << 26, v.size) / (1 << 26)      # 26 fraction bits, 2^11 times
+    w = w.astype(np.float32).astype(np.float64)
+    wh = _f16(w)
+    wl = _f16(w - wh)
+    wd = _f16(wh / 2048.0)
+    term = (wh * h + wl * h + wd * l) / 2048.0
+    exact = w / 2048.0 * v
+    near = np.maximum(w / 2048.0, 2.0 ** -13)                      # (a weight far below: next to nothing of its neighbour's)
+    assert (np.abs(term - exact)[big] <= 2.0 ** -20 * near[big] * np.abs(v[big])).all()
