@@ -663,7 +663,9 @@ PROFILE_CMDS = {
     "pmc": "rocprofv3 --pmc <COUNTER> --output-format csv -d <dir>/pmc_<name> -o pmc -- "
            "python -u bench.py --steps 1 --warmup 1 --no-cpu-baseline --quick-data --profile-only --calib-copy "
            "(one pass per counter: FETCH_SIZE, then WRITE_SIZE; then one pass of SQ_INSTS_VALU SQ_INSTS_LDS "
-           "SQ_LDS_BANK_CONFLICT SQ_ACTIVE_INST_LDS SQ_WAVES without --calib-copy, into <dir>/pmc_sq)",
+           "SQ_LDS_BANK_CONFLICT SQ_ACTIVE_INST_LDS SQ_WAVES SQ_INSTS_MFMA and one of SQ_VALU_MFMA_BUSY_CYCLES "
+           "SQ_LDS_IDX_ACTIVE SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_LDS GRBM_GUI_ACTIVE without --calib-copy, into "
+           "<dir>/pmc_sq and <dir>/pmc_busy)",
 }
 
 
@@ -675,7 +677,7 @@ def summarize_profiles(d):
     os.makedirs(out_dir, exist_ok=True)
 
     def short(name):
-        for key in ("bp2_kernel", "bp_kernel", "filter", "normalize_kernel", "copyBuffer", "fp_kernel"):
+        for key in ("bpm_kernel", "bp2_kernel", "bp_kernel", "filter", "normalize_kernel", "copyBuffer", "fp_kernel"):
             if key in name:
                 return name.replace("pyhst::(anonymous namespace)::", "").split("(")[0].replace("void ", "")
         return None
@@ -709,7 +711,7 @@ def summarize_profiles(d):
     log(f"wrote {txt}")
     # traffic: FETCH_SIZE / WRITE_SIZE (KiB) scaled by the same counters on a 2 GiB device copy
     cp = [k for k in counters if "copyBuffer" in k[0]]
-    bp = [k for k in counters if "bp2_kernel" in k[0]] or [k for k in counters if "bp_kernel" in k[0]]
+    bp = next((b for b in ([k for k in counters if n in k[0]] for n in ("bpm_kernel", "bp2_kernel", "bp_kernel")) if b), [])
     if cp and bp:
         copy_bytes = 2 * 2 ** 29 * 4
         cf = sum(counters[(cp[0][0], "FETCH_SIZE")]) / len(counters[(cp[0][0], "FETCH_SIZE")]) * 1024
@@ -718,8 +720,8 @@ def summarize_profiles(d):
         bname = bp[0][0]
         bf = sum(counters[(bname, "FETCH_SIZE")]) / len(counters[(bname, "FETCH_SIZE")]) * 1024
         bw = sum(counters[(bname, "WRITE_SIZE")]) / len(counters[(bname, "WRITE_SIZE")]) * 1024
-        rec = {"kernel": bname, "source_sha256_16": source_hash(os.path.join(ROOT, "paper_1306_1392_amd", "csrc",
-                                                                             "k_bp.hip")),
+        src = "k_bpm.hip" if "bpm_kernel" in bname else "k_bp.hip"
+        rec = {"kernel": bname, "source_sha256_16": source_hash(os.path.join(ROOT, "paper_1306_1392_amd", "csrc", src)),
                "fetch_scale": f_scale, "write_scale": w_scale,
                "fetch_bytes_per_launch": bf * f_scale, "write_bytes_per_launch": bw * w_scale,
                "hbm_bytes_per_launch": bf * f_scale + bw * w_scale,
